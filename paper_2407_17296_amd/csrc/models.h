@@ -30,23 +30,15 @@ namespace smc2 {
 // w * v with w = 0 giving 0 even for an infinite v: adjoint terms of particles whose weight or
 // state adjoint vanishes must contribute nothing (a select, not a branch).  In FP32 that is one
 // instruction, the multiplication with the rule 0 * anything = 0 (it holds for v = 0, too, also
-// under a w that is not finite); the compiler has no builtin for it and does not see that its
-// operands must not come straight from the transcendental unit (settled below).  Four such products
-// a particle and step with a comparison and selects: 1-D LG kernel (N 2048, M 512, T 250) 1.32 ms,
-// with this 1.29 ms.
-__device__ __forceinline__ float mulz(float w, float v) {
-  float d;
-  asm("v_mul_legacy_f32 %0, %1, %2" : "=v"(d) : "v"(w), "v"(v));
-  return d;
-}
+// under a w that is not finite).  HIP has no builtin for it, so the compiler's own operation is
+// declared by name: the compiler then sees what its operands are and keeps the wait state that a
+// result of the transcendental unit needs.  us with a comparison and selects / with this: 1-D LG
+// (N 2048, M 512, T 250) 1246 / 1230, growth (N 4096, M 512, T 100) 933 / 906, SV (64 series) 5268 /
+// 5146, 16-dimensional LG (N 512, M 2048, T 100) 4424 / 4249.
+extern "C" __device__ __attribute__((const)) float smc2_fmul_legacy(float, float)
+    __asm("llvm.amdgcn.fmul.legacy");
+__device__ __forceinline__ float mulz(float w, float v) { return smc2_fmul_legacy(w, v); }
 __device__ __forceinline__ double mulz(double w, double v) { return w == 0.0 ? 0.0 : w * v; }
-
-// A result of the transcendental unit, one wait state later.
-__device__ __forceinline__ float settled(float v) {
-  asm("s_nop 0" : "+v"(v));
-  return v;
-}
-__device__ __forceinline__ double settled(double v) { return v; }
 
 // a * b + c rounded once
 __device__ __forceinline__ float fmar(float a, float b, float c) {

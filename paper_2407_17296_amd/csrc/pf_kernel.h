@@ -1415,7 +1415,7 @@ void pf_fwd_adj_kernel(PFArgs A) {
               for (int p = 0; p < PPL; ++p) {
                 R v = (carried ? cl[p] : lWeqR) + mdl.weight_of(yv, xp[p], xn[p]);
                 if (!(v == v) || j0 + p >= M) v = (R)kNegInf;
-                wb[p] = settled(fexp(v - st, xk));
+                wb[p] = fexp(v - st, xk);
               }
             }
             if (res_t) scatter_to_parents(ca);
@@ -1539,7 +1539,7 @@ void pf_fwd_adj_kernel(PFArgs A) {
           if (t == T || res) {
             const ExpCoefs<R> xk;
 #pragma unroll
-            for (int p = 0; p < PPL; ++p) wv[p] = settled(fexp(wv[p] - st, xk));
+            for (int p = 0; p < PPL; ++p) wv[p] = fexp(wv[p] - st, xk);
             store_run<PPL>(row + DX * LD + j0, wv);
           }
           if (res) {
@@ -1630,7 +1630,7 @@ void pf_fwd_adj_kernel(PFArgs A) {
             if (t == T || res) {
               const ExpCoefs<R> xk;
 #pragma unroll
-              for (int p = 0; p < PPL; ++p) wv[p] = settled(fexp(wv[p] - st, xk));
+              for (int p = 0; p < PPL; ++p) wv[p] = fexp(wv[p] - st, xk);
               store_run<PPL>(row + WROW * LD + j0, wv);
             }
             if (res) {
