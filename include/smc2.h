@@ -113,7 +113,13 @@ typedef struct {
   double ess_frac;       /* resample after step t < T iff ESS < ess_frac * M (Sec. II-B: 0.5) */
   int32_t ckpt_interval; /* adjoint checkpoint interval c in steps; 0 = ceil(sqrt(T_max)) */
   int32_t want_grad;     /* 0: log-likelihood only; 1: also the gradient */
-  int32_t tile;          /* launch shape: 0 = tuned default, else an index from smc2_tile_info */
+  int32_t tile;          /* launch shape: 0 = tuned default, else an index from smc2_tile_info.
+                            The default goes by M and, in FP64, by S * N (few filters run on more
+                            waves each).  An FP64 estimate is the same bit for bit whichever of
+                            those shapes runs it, so it does not depend on S * N.  Gradients agree
+                            between shapes to rounding; they are the same from launch to launch
+                            on shapes of one wave and on the FP64 shapes of 256 particles, and to
+                            rounding (the order in which waves add to a parent) on the others. */
   int32_t persistent;    /* 1: persistent grid pulling (s, i) items longest-series-first from an
                             on-device queue; 0: one workgroup per item in the same order */
   int32_t store_noise;   /* 1: the forward sweep stores its reparameterised noise (drawn in

@@ -351,6 +351,8 @@ struct SysTargets {
 // parent marks the first offspring it owns, and an exclusive max-scan over the markers hands
 // every offspring the last parent that started at or before it; a reader
 // clears its own markers after use.  `dummy` is a per-lane marker slot for parents that own nothing.
+// Where a running sum goes over several lanes, it enters this one at `part0`, and `start` is
+// base + part0.
 //
 // The number of targets up to P is floor(z) + 1, z = P M / tot - nu, unless z lies so near an
 // integer that rounding decides.  z + 1.5 2^20 holds floor(z) in the low bits of its high word
@@ -364,9 +366,9 @@ struct SysTargets {
 // us, 1-D LG (N 2048, M 512, T 250, mixed) 1396 -> 1324 us.
 template <int WAVES, int PPL, typename R>
 __device__ __forceinline__ void systematic_ancestors(const SysTargets &tg, double scale,
-                                                     double base, const R (&ew)[PPL], int j0,
-                                                     int *sh_mark, int *sh_imax, int (&a)[PPL],
-                                                     int dummy) {
+                                                     double base, double part0, double start,
+                                                     const R (&ew)[PPL], int j0, int *sh_mark,
+                                                     int *sh_imax, int (&a)[PPL], int dummy) {
   constexpr double kMagic = 0x1.8p20;
   constexpr int kMagicHi = 0x41380000;
   auto split = [](double z, uint32_t &near) {
@@ -375,7 +377,7 @@ __device__ __forceinline__ void systematic_ancestors(const SysTargets &tg, doubl
     return (int)(b >> 32) - (kMagicHi - 1);
   };
   uint32_t near = 0xFFFFFFFFu;
-  double z = __builtin_fma(base, scale, 0x1p-29 - tg.nu);
+  double z = __builtin_fma(start, scale, 0x1p-29 - tg.nu);
   int prev = split(z, near);
   int cm[PPL];
 #pragma unroll
@@ -384,8 +386,8 @@ __device__ __forceinline__ void systematic_ancestors(const SysTargets &tg, doubl
     cm[p] = split(z, near);
   }
   if (near < 16u) {
-    prev = tg.upto(base);
-    double part = 0.0;
+    prev = tg.upto(start);
+    double part = part0;
 #pragma unroll
     for (int p = 0; p < PPL; ++p) {
       part += (double)ew[p];
@@ -442,6 +444,15 @@ void pf_fwd_adj_kernel(PFArgs A) {
   // the states on both sides of each step, the one before gathered from row t - 1 through the
   // stored ancestors, and recovers the step's noise from them instead of drawing it again.
   constexpr bool kPost = EVERY && !kWide;
+  // FP64 sums of the weights run over four consecutive particles, then over groups of four: the
+  // order of a lane with four particles, kept by the shapes that put fewer on a lane (kGroup lanes
+  // to a group), so that an estimate does not depend on which of them a launch runs on (the default
+  // shape goes by the number of filters).  One wave's parents also receive their offsprings'
+  // adjoints in a fixed order; four waves in its place take turns, so that a gradient is the same
+  // from launch to launch.
+  constexpr int kGroup =
+      sizeof(R) == 8 && !kWide && PPL < 4 && WAVES * PPL >= 4 ? 4 / PPL : 1;
+  constexpr bool kTurns = kGroup > 1 && WAVES * PPL == 4;
   // the multinomial prefix (MP doubles) or the systematic first-offspring markers with a dummy
   // per lane (MP + 64 ints): a launch uses one resampler, so the two share their LDS
   __shared__ double sh_pm[MP];
@@ -730,9 +741,32 @@ void pf_fwd_adj_kernel(PFArgs A) {
         qacc += ew[p] * ew[p];
         lW[p] = lW[p] - mxR;  // the carry: log-weights shifted by the maximum
       }
-      const double inc = wave_inclusive_sum(acc);
+      double part0 = 0.0;  // the group's particles on the lanes before (kGroup > 1)
+      if constexpr (kGroup > 1) group_sums<PPL>(ew, lane, acc, qacc, part0);
+      double inc = 0.0;
+      if constexpr (kGroup == 1) inc = wave_inclusive_sum(acc);
       double S = 0.0, Q = 0.0, off = 0.0;
-      if constexpr (WAVES == 1) {
+      if constexpr (kGroup > 1) {
+        // a run of kGroup waves has the groups that one wave of four particles a lane has, and is
+        // summed as that wave is, in a tree
+        const double sw = group_wave_sum<kGroup>(acc), qw = group_wave_sum<kGroup>(qacc);
+        if (lane == 63) {
+          ex[WAVES + 2 * wid] = sw;
+          ex[WAVES + 2 * wid + 1] = qw;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < WAVES; w += kGroup) {
+          const double *e = ex + WAVES + 2 * w;
+          if constexpr (kGroup == 2) {
+            S = S + (e[0] + e[2]);
+            Q = Q + (e[1] + e[3]);
+          } else {
+            S = S + ((e[0] + e[2]) + (e[4] + e[6]));
+            Q = Q + ((e[1] + e[3]) + (e[5] + e[7]));
+          }
+        }
+      } else if constexpr (WAVES == 1) {
         S = readlane_f64(inc, 63);
         Q = (double)wave_sum(qacc);
       } else {
@@ -782,7 +816,14 @@ void pf_fwd_adj_kernel(PFArgs A) {
       // prefix of the weights: P_j = (wave offset + lane prefix) + lane running sum to j
       R *sx = sh_X[nres & 1];
       ++nres;
-      const double base = off + dpp_f64<kDppWaveShr1>(0.0, inc);
+      double base, start;  // the prefix before the lane's group, and before its own particles
+      if constexpr (kGroup > 1) {
+        base = group_prefix<kGroup>(acc, ex + WAVES, lane);
+        start = base + part0;
+      } else {
+        base = off + dpp_f64<kDppWaveShr1>(0.0, inc);
+        start = base;
+      }
       const double tot = S;
 #pragma unroll
       for (int p = 0; p < PPL; ++p) sx[j0 + p] = x[p][0];
@@ -799,10 +840,10 @@ void pf_fwd_adj_kernel(PFArgs A) {
         tg.M = M;
         tg.Md = Md;
         tg.tot = tot;
-        systematic_ancestors<WAVES, PPL>(tg, rcp_mid(tot) * Md, base, ew, j0, sh_mark, sh_imax, a,
-                                         MP + lane);
+        systematic_ancestors<WAVES, PPL>(tg, rcp_mid(tot) * Md, base, part0, start, ew, j0,
+                                         sh_mark, sh_imax, a, MP + lane);
       } else {
-        double part = 0.0;
+        double part = part0;
 #pragma unroll
         for (int p = 0; p < PPL; ++p) {
           part += (double)ew[p];
@@ -854,7 +895,8 @@ void pf_fwd_adj_kernel(PFArgs A) {
     }
     {
       double part = 0.0;
-      for (int t = 1 + tid; t <= T; t += NT) {
+      constexpr int NS = NT / kGroup;  // as many threads as a shape of four particles a lane has
+      for (int t = 1 + (tid < NS ? tid : T); t <= T; t += NS) {
         const double lS = flog(g_s[t - 1]), m = g_mx[t - 1];
         part += (t == T || flg[t - 1]) ? m + lS : m;
         g_s[t - 1] = m + lS;
@@ -921,6 +963,28 @@ void pf_fwd_adj_kernel(PFArgs A) {
     // and each reader zeroes what it read; a set is written again only after the barrier of the
     // other set, which every reader of its previous use has passed.
     auto scatter_to_parents = [&](const int (&ca)[PPL]) {
+      if constexpr (kTurns) {
+        // the waves add one after the other, wave w component q in turn q + w: the order of the
+        // additions is fixed.  A component is complete, and read, after its last wave's turn; the
+        // next turn's barrier stands between those reads and the set's next use.
+        const int widu = wave_id_opaque();
+#pragma unroll
+        for (int turn = 0; turn < DX + WAVES - 1; ++turn) {
+#pragma unroll
+          for (int q = 0; q < DX; ++q)
+            if (turn - q == widu && j0 < M && xb[0][q] != (R)0)
+              atomicAdd(&sh_X[pp ^ (q & 1)][ca[0]], xb[0][q]);
+          __syncthreads();
+          const int q = turn - (WAVES - 1);
+          if (q >= 0) {
+            R *ss = sh_X[pp ^ (q & 1)];
+            xb[0][q] = ss[j0];
+            ss[j0] = (R)0;
+          }
+        }
+        pp ^= DX & 1;
+        return;
+      }
 #pragma unroll
       for (int q0 = 0; q0 < DX; q0 += SB) {
         const int set = pp;
