@@ -127,8 +127,7 @@ Prior make_prior(const smc2_model *m) {
   return pr;
 }
 
-// Default launch shape per particle count (largest particles-per-lane that keeps 4+ waves for
-// M >= 256; a single wave for the small filters).
+// Default launch shape per particle count and, in FP64, number of filters.
 int default_tile(int MP, int dx, int precision, int T_max, long items, int cus) {
   // tile indices refer to kTiles; measured on MI355X (fused forward+adjoint, systematic
   // resampling at most steps): one or two waves with 4 to 8 particles per lane for the 1-D
@@ -137,24 +136,25 @@ int default_tile(int MP, int dx, int precision, int T_max, long items, int cus) 
   // FP64 with few filters: the chip is not full, a launch takes as long as one filter does, and a
   // filter is faster on more waves with fewer particles a lane; with more filters than the lines
   // below the waves take turns and the wider shapes win.  us per launch, wider shape / more waves
-  // (T = 60, 256 compute units):
-  //                      1-D LG      growth, likelihood   SIR
-  //   256  N  256      202 / 165        127 / 112      148 / 86
-  //        N  512      217 / 194        132 / 137      151 / 101
-  //        N 1024      224 / 336        138 / 229      157 / 144
-  //        N 4096      647 / 1072       397 / 731      393 / 469
-  //   512  N  256      232 / 198        147 / 131      168 / 115
-  //        N  512      311 / 247        203 / 167      208 / 140
-  //        N 1024      355 / 433        226 / 307      231 / 240
-  //  1024  N  256                                      185 / 158
-  //        N  512                                      235 / 292
+  // (T = 60, 256 compute units, gradient with ceil(sqrt T) checkpoints, growth likelihoods only; a
+  // checkpoint at every step and T = 300 give the same signs):
+  //                  1-D LG     optimal       SV        growth      SIR      SIR, likelihood
+  //   250  N   64   227 / 190  194 / 137  224 / 154   118 / 108  267 / 186     125 / 103
+  //        N  256   231 / 193  197 / 139  229 / 156   121 / 111  275 / 197     128 / 107
+  //        N  384   239 / 234  203 / 174  234 / 196   124 / 133  285 / 238     130 / 129
+  //        N  512   240 / 236  205 / 176  236 / 198   125 / 134  290 / 240     131 / 129
+  //        N 1024   257 / 337  205 / 303  235 / 343   124 / 227  335 / 403     132 / 219
+  //   500  N  256   266 / 230  217 / 170  254 / 188   147 / 126  313 / 236     150 / 122
+  //        N  512   359 / 289  311 / 229  363 / 252   201 / 160  449 / 316     216 / 159
+  //        N 1024   423 / 497  342 / 394  391 / 440   213 / 273  544 / 535     235 / 268
+  //  1000  N   64   288 / 304  221 / 229  255 / 257   154 / 173  321 / 310     154 / 167
+  //        N  256   295 / 312  226 / 234  261 / 262   157 / 177  363 / 364     160 / 173
+  // so the two shapes of 1024 particles do not differ where the chip is not full.
   // (The mixed form keeps one shape per particle count: its FP32 sums take their order from it.
   // Series near the end of the LDS staging keep the shape with the smaller arrays.)
   if (precision == SMC2_FP64 && T_max <= 8192) {
-    if (MP == 256 && ((dx == 1 && items <= cus) || (dx == 2 && items <= 4l * cus)))
-      return 4;  // {4, 1}
-    if (MP == 512 && dx <= 2 && items <= 2l * cus) return 7;  // {4, 2}
-    if (MP == 1024 && dx == 2 && items <= cus) return 11;     // {8, 2}
+    if (MP == 256 && dx <= 2 && items <= (long)dx * cus) return 4;  // {4, 1}
+    if (MP == 512 && dx <= 2 && items <= 2l * cus) return 7;        // {4, 2}
   }
   if (dx == 2) {  // the SIR model: one particle per lane up to 128, then four
     switch (MP) {
