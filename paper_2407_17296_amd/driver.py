@@ -34,6 +34,23 @@ class Records:
     p_prev: np.ndarray             # [K][S][N][D] velocities drawn by the move
 
 
+def _population(shapes, **kw):
+    """One zeroed buffer and its consecutive views of the given shapes."""
+    sizes = [int(np.prod(s)) for s in shapes.values()]
+    flat = torch.zeros(sum(sizes), **kw)
+    return flat, {k: v.view(s) for v, (k, s) in zip(torch.split(flat, sizes), shapes.items())}
+
+
+def _is_whole(pop, flat):
+    """Whether the arrays of a population are still the consecutive views that make up its buffer."""
+    at = flat.data_ptr()
+    for v in pop.values():
+        if v.data_ptr() != at or not v.is_contiguous():
+            return False
+        at += v.numel() * flat.element_size()
+    return at == flat.data_ptr() + flat.numel() * flat.element_size()
+
+
 class SMC2Run:
     """Device state of one SMC^2 run: two populations, the move's velocities, the counter."""
 
@@ -57,13 +74,8 @@ class SMC2Run:
         # copy: five copies took 23 of the 110 us of a small iteration (N = 32, M = 64, T = 50)
         shapes = dict(theta=(S, N, D), logpost=(S, N), grad_logpost=(S, N, D), loglik=(S, N),
                       logw=(S, N))
-
-        def pop():
-            flat = torch.zeros(S * N * (2 * D + 3), **f64)
-            parts = torch.split(flat, [int(np.prod(s)) for s in shapes.values()])
-            return flat, {k: v.view(s) for v, (k, s) in zip(parts, shapes.items())}
-        self._cur_flat, self.cur = pop()
-        self._prev_flat, self.prev = pop()
+        self._cur_flat, self.cur = _population(shapes, **f64)
+        self._prev_flat, self.prev = _population(shapes, **f64)
         self.p_prev = torch.zeros((S, N, D), **f64)
         self.y = torch.tensor(w.y, **f64).contiguous()
         self.iteration = torch.ones(1, dtype=torch.int32, device=self.dev)
@@ -98,7 +110,11 @@ class SMC2Run:
                                 self.iteration, self.cur["theta"], self.p_prev, stream=stream)
 
     def _carry(self):
-        self._prev_flat.copy_(self._cur_flat)
+        if _is_whole(self.cur, self._cur_flat) and _is_whole(self.prev, self._prev_flat):
+            self._prev_flat.copy_(self._cur_flat)
+            return
+        for key in self.cur:  # an array was replaced or added: array by array
+            self.prev[key].copy_(self.cur[key])
 
     def first_iteration(self):
         """k = 1: theta ~ prior, filter, weights = likelihood, normalise, ESS, resample."""
