@@ -31,3 +31,22 @@ def test_fp64_wide_scatter(oracle, M, tile, ckpt, store_noise, resampler):
         assert same.any()
         rel = np.linalg.norm(g32 - g, axis=-1) / np.linalg.norm(g, axis=-1)
         assert np.all(rel[same] <= 1e-3)
+
+
+@pytest.mark.parametrize("store_noise", [0, 1])
+@pytest.mark.parametrize("M,tile", [(1, 1), (60, 1), (65, 2), (128, 2), (250, 4), (500, 7), (1024, 11),
+                                    (2047, 14), (2047, 17), (2048, 17)])
+@pytest.mark.parametrize("resampler", [smc2.SYSTEMATIC, smc2.MULTINOMIAL])
+def test_mixed_wide_segments_against_every_step(M, tile, store_noise, resampler):
+    """The mixed form's segments against its own every-step checkpoints, on every shape: the forward
+    sweep is the same, so the estimates agree bit for bit, whatever ancestors they take, and the
+    gradients to rounding (their sums take another order)."""
+    w = synth.make(2, N=3, M=M, T=6)
+    theta = np.broadcast_to(w.theta_true, (1, 3, w.D)).copy()
+    theta[0, :, -1] = [3.0, 0.5, -1.5]
+    kw = dict(precision=smc2.MIXED, tile=tile, k=4, resampler=resampler, ess_frac=1.5)
+    ll, g, _ = gpu_pf(w, theta, ckpt=1, store_noise=store_noise, **kw)
+    ll4, g4, _ = gpu_pf(w, theta, ckpt=4, store_noise=store_noise, **kw)
+    assert np.array_equal(ll, ll4)
+    rel = np.linalg.norm(g4 - g, axis=-1) / np.linalg.norm(g, axis=-1)
+    assert np.all(rel <= 1e-4), rel
