@@ -21,3 +21,10 @@ def test_multinomial_search(oracle, M, tile):
     ll, g, tr = gpu_pf(w, theta, tile=tile, ckpt=1, k=2, resampler=smc2.MULTINOMIAL,
                        ess_frac=1.5, trace_items=items)
     _check_fp64(oracle, w, theta, ll, g, tr, k=2, resampler=smc2.MULTINOMIAL, ess_frac=1.5)
+
+
+@pytest.mark.parametrize("M,tile", [(200, 4), (511, 7), (512, 7), (1000, 8), (1024, 8), (1023, 11),
+                                    (2047, 12), (2048, 12), (2049, 15), (4095, 15), (4096, 16)])
+def test_multinomial_search_in_chunks(oracle, M, tile):
+    """The same on lanes of one and two slots, and of sixteen (two chunks of eight searches)."""
+    test_multinomial_search(oracle, M, tile)
