@@ -31,3 +31,19 @@ def test_fp64_noise_groups(oracle, index, M, tile, ckpt, store_noise):
     ll32, _, _ = gpu_pf(w, theta, precision=smc2.MIXED, tile=tile, ckpt=ckpt, k=5,
                         store_noise=store_noise)
     assert (abs(ll32 - ll) <= 1e-4 * 10).mean() >= 0.3
+
+
+@pytest.mark.parametrize("ckpt,store_noise", [(1, 0), (3, 0), (3, 1)])
+@pytest.mark.parametrize("index,M,tile", [(0, 64, 1), (0, 100, 2), (0, 256, 4), (0, 512, 7), (0, 200, 3),
+                                          (0, 500, 5), (5, 60, 1), (5, 256, 4), (5, 200, 3)])
+def test_mixed_noise_groups(index, M, tile, ckpt, store_noise):
+    """The mixed form draws the same words: without resampling no ancestor can flip, and every estimate
+    and gradient follows the FP64 form's."""
+    w = synth.make(index, N=16, M=M, T=10)
+    theta = spread_theta(w, 0.05, seed=90 + M)
+    kw = dict(tile=tile, ckpt=ckpt, k=5, store_noise=store_noise, ess_frac=0.0)
+    ll, g, _ = gpu_pf(w, theta, **kw)
+    ll32, g32, _ = gpu_pf(w, theta, precision=smc2.MIXED, **kw)
+    assert abs(ll32 - ll).max() <= 1e-4 * 10
+    for i in range(w.N):
+        assert ((g32[0, i] - g[0, i]) ** 2).sum() <= (1e-3 ** 2) * (g[0, i] ** 2).sum()
