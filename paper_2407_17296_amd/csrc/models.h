@@ -145,52 +145,11 @@ struct ModelLGDiag : Bootstrap<ModelLGDiag<R, D_X>, R> {
     isy = (R)exp(-th[D_X + 1]);
   }
   __device__ void per_step(int) {}
-  __device__ void init(const R *e0, R *x) const {
-#pragma unroll
-    for (int q = 0; q < D_X; ++q) x[q] = e0[q];
-  }
   __device__ void init_adj(const R *, const R *, double *) const {}
-  __device__ void step(R *x, const R *e) const {
-#pragma unroll
-    for (int q = 0; q < D_X; ++q) x[q] = fmar(A[q], x[q], sx * e[q]);
-  }
-  template <typename Acc>
-  __device__ void step_adj(const R *xp, const R *e, R *xb, Acc *tb) const {
-    R ssx = (R)0;
-#pragma unroll
-    for (int q = 0; q < D_X; ++q) {
-      tb[q] += (Acc)mulz(xb[q], xp[q]);
-      ssx += mulz(xb[q], e[q]);
-      xb[q] = A[q] * xb[q];
-    }
-    tb[D_X] += (Acc)(ssx * sx);
-  }
-  __device__ R logg(const R *y, const R *x) const {
-    R s2 = (R)0;
-#pragma unroll
-    for (int q = 0; q < D_X; ++q) {
-      const R r = (y[q] - x[q]) * isy;
-      s2 = fmar(r, r, s2);
-    }
-    return fmar((R)-0.5, s2, c0);
-  }
-  template <typename Acc>
-  __device__ void logg_adj(const R *y, const R *x, R wb, R *xb, Acc *tb) const {
-    R s2 = (R)0;
-#pragma unroll
-    for (int q = 0; q < D_X; ++q) {
-      const R r = (y[q] - x[q]) * isy;
-      xb[q] += mulz(wb, r * isy);
-      s2 = fmar(r, r, s2);
-    }
-    tb[D_X + 1] += (Acc)mulz(wb, s2 - (R)D_X);
-  }
 
-  // Blockwise form, for streaming a particle through a step four components at a time
-  // (components 4b .. 4b + 3): given theta the components are independent, and log g couples
-  // them only through its sum of squared residuals.  Taking the blocks in order reproduces the
-  // sums of step / logg / logg_adj / step_adj bit for bit.
-  static constexpr bool kBlocks = true;
+  // A particle goes through a step four components at a time (components 4b .. 4b + 3): given theta
+  // the components are independent, and log g couples them only through its sum of squared
+  // residuals.
   // the start of a block from its noise
   __device__ void init_block(int, const R (&e4)[4], R (&x4)[4]) const {
 #pragma unroll

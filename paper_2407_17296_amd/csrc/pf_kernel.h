@@ -465,11 +465,10 @@ void pf_fwd_adj_kernel(PFArgs A) {
   __shared__ double sh_ex[2][3 * WAVES];  // per-wave max and (sum, sum of squares), ping-pong
   __shared__ double sh_vec[WAVES * NP];
   __shared__ double sh_tb[kWide ? WAVES * NP : 1];  // per-wave parameter adjoint (wide states)
-  // wide states: each lane's running sums of the blocks'
-  // parameter adjoints (four per block) wait in LDS between the steps, as [block][lane][4],
-  // where they fit in 64 KiB
-  constexpr bool kTaLds = kWide && DX * NT * sizeof(R) <= 65536;
-  __shared__ __align__(16) R sh_ta[kTaLds ? DX * NT : 4];
+  // wide states: each lane's running sums of the blocks' parameter adjoints (four per block) wait in
+  // LDS between the steps, as [block][lane][4]
+  static_assert(!kWide || DX * NT * sizeof(R) <= 65536, "the parameter adjoints' LDS");
+  __shared__ __align__(16) R sh_ta[kWide ? DX * NT : 4];
   __shared__ __align__(16) R sh_model[Model::kShared > 0 ? Model::kShared : 1];
   __shared__ int sh_imax[WAVES];
   __shared__ int sh_item;
@@ -1101,31 +1100,33 @@ void pf_fwd_adj_kernel(PFArgs A) {
     // observation and transition are differentiated.  xp / xn: state before / after the step.
     auto reverse_step = [&](int t, const R (&xp)[PPL][DX], const R (&ce)[PPL][DX],
                             const R (&cw)[PPL], const int (&ca)[PPL]) {
-      const R *yv = sh_y + (size_t)(t - 1) * DY;
-      win(t);
-      const bool res = t < T && flag_of(t);
-      if (t == T) {
+      if constexpr (!kWide) {
+        const R *yv = sh_y + (size_t)(t - 1) * DY;
+        win(t);
+        const bool res = t < T && flag_of(t);
+        if (t == T) {
 #pragma unroll
-        for (int p = 0; p < PPL; ++p) wb[p] = cw[p];
-      } else if (res) {
-        scatter_to_parents(ca);
+          for (int p = 0; p < PPL; ++p) wb[p] = cw[p];
+        } else if (res) {
+          scatter_to_parents(ca);
 #pragma unroll
-        for (int p = 0; p < PPL; ++p) wb[p] = cw[p];
+          for (int p = 0; p < PPL; ++p) wb[p] = cw[p];
+        }
+        // the lane's particles add their parameter adjoints in R; the step total joins the FP64
+        // accumulator
+        R tp[NP];
+#pragma unroll
+        for (int k = 0; k < NP; ++k) tp[k] = (R)0;
+#pragma unroll
+        for (int p = 0; p < PPL; ++p) {
+          R xn[DX];  // the state after the step, rebuilt where the adjoint needs it
+#pragma unroll
+          for (int q = 0; q < DX; ++q) xn[q] = xp[p][q];
+          (void)mdl.advance(xn, ce[p], yv);
+          mdl.advance_adj(yv, xp[p], xn, ce[p], wb[p], xb[p], tp);
+        }
+        add_step_adjoint(tp);
       }
-      // the lane's particles add their parameter adjoints in R; the step total joins the FP64
-      // accumulator
-      R tp[NP];
-#pragma unroll
-      for (int k = 0; k < NP; ++k) tp[k] = (R)0;
-#pragma unroll
-      for (int p = 0; p < PPL; ++p) {
-        R xn[DX];  // the state after the step, rebuilt where the adjoint needs it
-#pragma unroll
-        for (int q = 0; q < DX; ++q) xn[q] = xp[p][q];
-        (void)mdl.advance(xn, ce[p], yv);
-        mdl.advance_adj(yv, xp[p], xn, ce[p], wb[p], xb[p], tp);
-      }
-      add_step_adjoint(tp);
     };
     auto zero_staging = [&]() {
       __syncthreads();  // earlier readers of the staging are done
@@ -1157,7 +1158,7 @@ void pf_fwd_adj_kernel(PFArgs A) {
     auto ta_row = [&](int b) -> R(&)[4] {
       return *reinterpret_cast<R(*)[4]>(&sh_ta[((size_t)b * NT + tid) * 4]);
     };
-    if constexpr (kTaLds) {
+    if constexpr (kWide) {
 #pragma unroll
       for (int b = 0; b < DX / 4; ++b)
 #pragma unroll
@@ -1219,7 +1220,7 @@ void pf_fwd_adj_kernel(PFArgs A) {
             for (int b = 0; b < DX / 4; ++b) {
               R ta[4];
 #pragma unroll
-              for (int i = 0; i < 4; ++i) ta[i] = kTaLds ? ta_row(b)[i] : tpl[4 * b + i];
+              for (int i = 0; i < 4; ++i) ta[i] = ta_row(b)[i];
               // the block's states before the step, a row of each component at a time (the lane's
               // particles are neighbours: one load)
               R xr[4][PPL], er[4][PPL];
@@ -1270,12 +1271,7 @@ void pf_fwd_adj_kernel(PFArgs A) {
                 if constexpr (sizeof(R) == 8) __builtin_amdgcn_sched_barrier(0);
               }
 #pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                if constexpr (kTaLds)
-                  ta_row(b)[i] = ta[i];
-                else
-                  tpl[4 * b + i] = ta[i];
-              }
+              for (int i = 0; i < 4; ++i) ta_row(b)[i] = ta[i];
             }
           };
           if (noise)
@@ -1288,11 +1284,9 @@ void pf_fwd_adj_kernel(PFArgs A) {
 #pragma unroll
             for (int k = 0; k < NP; ++k) {
               R v = tpl[k];
-              if constexpr (kTaLds) {
-                if (k < DX) {
-                  v = ta_row(k / 4)[k % 4];
-                  ta_row(k / 4)[k % 4] = (R)0;
-                }
+              if (k < DX) {
+                v = ta_row(k / 4)[k % 4];
+                ta_row(k / 4)[k % 4] = (R)0;
               }
               if constexpr (kFlush == 1 && PPL == 1) {  // room for the lane's own sums
                 tb[k] += (double)v;
