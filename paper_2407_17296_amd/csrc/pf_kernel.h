@@ -910,13 +910,13 @@ void pf_fwd_adj_kernel(PFArgs A) {
     __syncthreads();  // the per-step log normalisers are visible to the workgroup
     // The per-step scalars the sweeps below read at every step (resampling flag, max_t + log
     // S_t, max_t) come from a window of 64 aligned steps, one step per lane, loaded once per 64
-    // steps: the flags as a wave ballot (with the 64 steps before the window, for the flag of
-    // the step before), the others read back with readlane.  The step index is uniform, so
+    // steps: the flags as a wave ballot (with the 64 steps before the window, for the flags of
+    // steps t - 1 and t - 2), the others read back with readlane.  The step index is uniform, so
     // every read of the window is too.
     int wbase = -(1 << 30);
     uint64_t wfl = 0, wfl_lo = 0;
     R wst = (R)0, wmt = (R)0;
-    auto win = [&](int t) {  // makes the scalars of steps t and t - 1 readable (1 <= t <= T)
+    auto win = [&](int t) {  // step t's scalars and the flags back to t - 2 (1 <= t <= T)
       const int b = (t - 1) & ~63;
       if (b != wbase) {
         wbase = b;
@@ -1149,8 +1149,9 @@ void pf_fwd_adj_kernel(PFArgs A) {
     // four components of every particle of the lane at a time: the block's state before the
     // step (checkpoint) and noise are read, the block's step rebuilt and differentiated.  The
     // weight adjoint restarts from the normalised weights the forward stored.  The lane's
-    // parameter adjoint is summed in R over 16 steps at a time (the blocks' parts in LDS where
-    // they fit), then over the wave in FP64 into its LDS row.
+    // parameter adjoint is summed in R (the blocks' parts in LDS) over kFlush steps at a time, 16
+    // or, for FP32 segments, one; a flush adds it to the lane's FP64 sums (FP32 segments, one particle
+    // a lane) or, over the wave, to its FP64 row in LDS.
     constexpr int kFlush = (EVERY || sizeof(R) == 8) ? 16 : 1;
     R tpl[NP];
 #pragma unroll
