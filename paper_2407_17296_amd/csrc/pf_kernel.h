@@ -895,7 +895,9 @@ void pf_fwd_adj_kernel(PFArgs A) {
     {
       double part = 0.0;
       constexpr int NS = NT / kGroup;  // as many threads as a shape of four particles a lane has
-      for (int t = 1 + (tid < NS ? tid : T); t <= T; t += NS) {
+      int first = 1 + tid;
+      if constexpr (kGroup > 1) first = tid < NS ? first : T + 1;
+      for (int t = first; t <= T; t += NS) {
         const double lS = flog(g_s[t - 1]), m = g_mx[t - 1];
         part += (t == T || flg[t - 1]) ? m + lS : m;
         g_s[t - 1] = m + lS;
