@@ -78,7 +78,7 @@ struct PFArgs {
                         // wide states: ckpt times x and the weight, then the steps' noise
   void *noise;          // [slots][t_ld+1][DX][ld] (R) forward noise for the adjoint, or NULL
   double *steps_s;      // [slots][t_ld] the per-step log normalisers s_t (a trace), or NULL
-  double *step_scr;     // [slots][2][t_ld]: S_t (after the sweep max_t + log S_t), max_t
+  double *step_scr;     // [slots][2][t_ld]: S_t (after the sweep log S_t), max_t
   double mconst[4];     // model constants (the SIR model's N_pop, I_0, s_e^2, s_y)
 };
 
@@ -544,7 +544,7 @@ void pf_fwd_adj_kernel(PFArgs A) {
     R *ck = (R *)A.ckpt_buf + (size_t)slot * A.nseg_max * (DX + 1) * LD;
     int32_t *anc = A.anc + (size_t)slot * A.t_ld * LD;
     uint8_t *flg = A.flags + (size_t)slot * A.t_ld;
-    // per-step scalars of the item: S_t (max_t + log S_t once the sweep is done) and max_t
+    // per-step scalars of the item: S_t (log S_t once the sweep is done) and max_t
     double *g_s = A.step_scr + (size_t)slot * 2 * A.t_ld;
     double *g_mx = g_s + A.t_ld;
     R *nz = A.noise ? (R *)A.noise + (size_t)slot * (A.t_ld + 1) * DX * LD : nullptr;
@@ -877,21 +877,9 @@ void pf_fwd_adj_kernel(PFArgs A) {
       if (gout && tid < NP) gout[tid] = 0.0;
       continue;
     }
-    // loglik = sum_t max_t + sum over resampled steps and T of log S_t; the adjoint's per-step
-    // log normaliser max_t + log S_t replaces S_t in LDS
+    // loglik = sum_t max_t + sum over resampled steps and T of log S_t; log S_t, taken once a step,
+    // replaces S_t
     __syncthreads();  // S_t, max_t and the flags written by thread 0 are visible
-    if (A.steps_s) {
-      // the trace of s_t = log sum_j W_{t-1}^j g_t^j with normalised W_{t-1} (eq.
-      // likelihood_pf_ step by step): the carry into step t was normalised at t = 1 and after a
-      // resampling step, and otherwise sums to S_{t-1}
-      double *so = A.steps_s + (size_t)slot * A.t_ld;
-      for (int t = 1 + tid; t <= T; t += NT) {
-        double v = g_mx[t - 1] + flog(g_s[t - 1]);
-        if (t > 1 && !flg[t - 2]) v -= flog(g_s[t - 2]);
-        so[t - 1] = v;
-      }
-      __syncthreads();  // every S_t is read before the loop below overwrites it
-    }
     {
       double part = 0.0;
       constexpr int NS = NT / kGroup;  // as many threads as a shape of four particles a lane has
@@ -900,16 +888,27 @@ void pf_fwd_adj_kernel(PFArgs A) {
       for (int t = first; t <= T; t += NS) {
         const double lS = flog(g_s[t - 1]), m = g_mx[t - 1];
         part += (t == T || flg[t - 1]) ? m + lS : m;
-        g_s[t - 1] = m + lS;
+        g_s[t - 1] = lS;
       }
       double v[1] = {part};
       block_sum_vec<WAVES, 1>(v, sh_vec);
       if (tid == 0) A.loglik[item] = v[0];
     }
+    __syncthreads();  // the logarithms are visible to the workgroup
+    if (A.steps_s) {
+      // the trace of s_t = log sum_j W_{t-1}^j g_t^j with normalised W_{t-1} (eq.
+      // likelihood_pf_ step by step): the carry into step t was normalised at t = 1 and after a
+      // resampling step, and otherwise sums to S_{t-1}
+      double *so = A.steps_s + (size_t)slot * A.t_ld;
+      for (int t = 1 + tid; t <= T; t += NT) {
+        double v = g_mx[t - 1] + g_s[t - 1];
+        if (t > 1 && !flg[t - 2]) v -= g_s[t - 2];
+        so[t - 1] = v;
+      }
+    }
     if (!A.want_grad) continue;
 
     // ---- adjoint --------------------------------------------------------------------------
-    __syncthreads();  // the per-step log normalisers are visible to the workgroup
     // The per-step scalars the sweeps below read at every step (resampling flag, max_t + log
     // S_t, max_t) come from a window of 64 aligned steps, one step per lane, loaded once per 64
     // steps: the flags as a wave ballot (with the 64 steps before the window, for the flags of
@@ -925,8 +924,9 @@ void pf_fwd_adj_kernel(PFArgs A) {
         const int i = b + lane, il = b - 64 + lane;
         wfl = __ballot(i < T && flg[i] != 0);
         wfl_lo = __ballot(il >= 0 && flg[il] != 0);
-        wst = i < T ? (R)g_s[i] : (R)0;
-        wmt = i < T ? (R)g_mx[i] : (R)0;
+        const double m = i < T ? g_mx[i] : 0.0;
+        wst = i < T ? (R)(m + g_s[i]) : (R)0;
+        wmt = (R)m;
       }
     };
     auto flag_of = [&](int t) -> bool {  // step t in [wbase - 63, wbase + 64]
